@@ -23,8 +23,13 @@ struct DevMesh {
     const int32_t* t_new2old; // [nt]
     const int32_t* t_old2new; // [nt]
     const int32_t* seed;      // [G^3]
+    const uint8_t* clear;     // [R0*R1*R2] clearance grid (pack.h), or null: the mesh has none
     float lo[3];
     float inv_cell[3];
+    float clear_inv[3];       // clearance cells per unit length
+    float R[3];               // clearance cells per axis
+    int32_t clear_cells;      // ... and in all
+    int32_t clear_passes;     // cells a ray can cross, at most
     int32_t G;
     int32_t nt;
     int32_t np;
@@ -92,6 +97,7 @@ struct LaunchCfg {
     int32_t xcds;           // one lane per ray: XCDs the blocks are renumbered for (1 = off)
     int32_t xcd_blocks;     // consecutive blocks per XCD (0 = one contiguous range each)
     float eps;              // > 0: precision variant (one lane per ray)
+    bool clear;             // the walk may use the mesh's clearance grid (no step counts, default cap)
     Queue queue;            // kernel 3
     struct Job* queue_job;  // kernel 3: device room for a one-entry job table
     uint32_t* defer_count;  // eps > 0, non-null: two passes (counter and list of deferred rays)

@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <limits>
+#include <mutex>
 #include <thread>
 
 namespace tetrt {
@@ -82,6 +83,177 @@ double orient3d(const float* P, const int32_t* t) {
     double cx = double(c[0]) - a[0], cy = double(c[1]) - a[1], cz = double(c[2]) - a[2];
     double dx = double(d[0]) - a[0], dy = double(d[1]) - a[1], dz = double(d[2]) - a[2];
     return bx * (cy * dz - cz * dy) - by * (cx * dz - cz * dx) + bz * (cx * dy - cy * dx);
+}
+
+// Whether triangle p (cell coordinates) meets the box of half-extents h about c:
+// separating axes (the box's, the plane, the nine edge products).
+bool triangle_meets_box(const double p[3][3], const double c[3], const double h[3]) {
+    double v[3][3];
+    for (int k = 0; k < 3; ++k)
+        for (int a = 0; a < 3; ++a) v[k][a] = p[k][a] - c[a];
+    for (int a = 0; a < 3; ++a)
+        if (std::min({v[0][a], v[1][a], v[2][a]}) > h[a] || std::max({v[0][a], v[1][a], v[2][a]}) < -h[a])
+            return false;
+    double e[3][3];
+    for (int k = 0; k < 3; ++k)
+        for (int a = 0; a < 3; ++a) e[k][a] = v[(k + 1) % 3][a] - v[k][a];
+    auto apart = [&](const double x[3]) {
+        double lo = 0.0, hi = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            const double s = x[0] * v[k][0] + x[1] * v[k][1] + x[2] * v[k][2];
+            lo = k ? std::min(lo, s) : s;
+            hi = k ? std::max(hi, s) : s;
+        }
+        const double r = h[0] * std::fabs(x[0]) + h[1] * std::fabs(x[1]) + h[2] * std::fabs(x[2]);
+        return lo > r || hi < -r;
+    };
+    const double n[3] = {e[0][1] * e[1][2] - e[0][2] * e[1][1], e[0][2] * e[1][0] - e[0][0] * e[1][2],
+                         e[0][0] * e[1][1] - e[0][1] * e[1][0]};
+    if (apart(n)) return false;
+    for (int k = 0; k < 3; ++k) {
+        const double x[3][3] = {{0.0, -e[k][2], e[k][1]}, {e[k][2], 0.0, -e[k][0]}, {-e[k][1], e[k][0], 0.0}};
+        for (int a = 0; a < 3; ++a)
+            if (apart(x[a])) return false;
+    }
+    return true;
+}
+
+// The clearance grid of a mesh that fills its bounding box, so that a ray inside
+// the box is inside the mesh and a ray that leaves the box leaves the mesh.  That
+// holds when every boundary face lies in a plane of the box (compared exactly) and
+// the tets' volumes add up to the box's: they cover it at least once, so equal
+// volumes leave no room for an overlap.  Other meshes get no grid (out->clear
+// empty) and are walked from tet to tet throughout.  A cell counts as touched when
+// a constrained triangle comes within kClearPad cells of it: more than the
+// rounding of a float32 position along a ray.
+constexpr double kClearPad = 4e-3;
+constexpr double kClearRound = 2e-4;         // cells a float32 position may be off by
+constexpr double kClearMaxAxis = 1024.0;
+// Cell size in cubes of six tets.  Smaller cells leave less of the scene touched
+// and more passes through the grid: occlusion rays of the 12.6M-tet scene 887 / 806 /
+// 835 us with 1.0 / 0.7 / 0.5, camera rays 121 / 109 / 130 us (one run each).
+constexpr double kClearCell = 0.7;
+constexpr int64_t kClearMaxCells = int64_t(1) << 24;
+
+void clearance_grid(const float* P, const int32_t* tets, const int32_t* nbrs, int64_t nt,
+                    const std::vector<int32_t>& tri, const float lo[3], const float hi[3], PackedMesh* out) {
+    out->clear.clear();
+    double ext[3], box = 1.0;
+    for (int a = 0; a < 3; ++a) {
+        ext[a] = double(hi[a]) - double(lo[a]);
+        box *= ext[a];
+    }
+    if (!(box > 0.0) || !std::isfinite(box)) return;
+    std::atomic<bool> ok{true};
+    std::vector<double> part;
+    std::mutex mu;
+    parallel_for(nt, [&](int64_t b, int64_t e) {
+        double v6 = 0.0;
+        bool good = true;
+        for (int64_t t = b; t < e && good; ++t) {
+            v6 += std::fabs(orient3d(P, tets + 4 * t));
+            for (int j = 0; j < 4; ++j) {
+                if (nbrs[4 * t + j] >= 0) continue;
+                bool flat = false;
+                for (int a = 0; a < 3; ++a) {
+                    bool l = true, h = true;
+                    for (int s = 0; s < 4; ++s) {
+                        if (s == j) continue;
+                        const float x = P[3 * int64_t(tets[4 * t + s]) + a];
+                        l = l && x == lo[a];
+                        h = h && x == hi[a];
+                    }
+                    flat = flat || l || h;
+                }
+                good = good && flat;
+            }
+        }
+        if (!good) ok = false;
+        std::lock_guard<std::mutex> g(mu);
+        part.push_back(v6);
+    });
+    double v6 = 0.0;
+    for (double x : part) v6 += x;
+    if (!ok || !(std::fabs(v6 / 6.0 - box) <= 1e-8 * box)) return;
+
+    // cells somewhat smaller than a cube of six tets (kClearCell)
+    const double side = kClearCell * std::cbrt(box * 6.0 / double(nt));
+    int64_t cells = 1;
+    int32_t R[3];
+    for (int a = 0; a < 3; ++a) {
+        R[a] = int32_t(std::max(1.0, std::min(kClearMaxAxis, std::round(ext[a] / side))));
+        cells *= R[a];
+    }
+    if (cells > kClearMaxCells) {
+        const double f = std::cbrt(double(kClearMaxCells) / double(cells));
+        cells = 1;
+        for (int a = 0; a < 3; ++a) {
+            R[a] = std::max(1, int32_t(R[a] * f));
+            cells *= R[a];
+        }
+        if (cells > kClearMaxCells) return;   // a box so flat that one axis has a single cell
+    }
+    // float32 positions have to be much finer than kClearPad cells
+    float inv[3];
+    for (int a = 0; a < 3; ++a) {
+        inv[a] = float(R[a] / ext[a]);
+        const double big = std::max(std::fabs(double(lo[a])), std::fabs(double(hi[a])));
+        if (!(big * std::ldexp(1.0, -23) * inv[a] <= kClearRound)) return;
+    }
+    // triangles to cells
+    std::vector<uint8_t> D(size_t(cells), 255);
+    const int64_t ntri = int64_t(tri.size()) / 3;
+    const double half[3] = {0.5 + kClearPad, 0.5 + kClearPad, 0.5 + kClearPad};
+    std::atomic<int64_t> budget{64 * cells + 64 * ntri + (int64_t(1) << 20)};   // box tests
+    parallel_for(ntri, [&](int64_t b, int64_t e) {
+        for (int64_t f = b; f < e; ++f) {
+            double p[3][3];
+            int32_t c0[3], c1[3];
+            int64_t tests = 1;
+            for (int a = 0; a < 3; ++a) {
+                for (int k = 0; k < 3; ++k)
+                    p[k][a] = (double(P[3 * int64_t(tri[3 * f + k]) + a]) - double(lo[a])) * double(inv[a]);
+                const double l = std::min({p[0][a], p[1][a], p[2][a]}) - kClearPad;
+                const double h = std::max({p[0][a], p[1][a], p[2][a]}) + kClearPad;
+                c0[a] = std::max(0, int32_t(std::floor(l)));
+                c1[a] = std::min(R[a] - 1, int32_t(std::floor(h)));
+                tests *= std::max(0, c1[a] - c0[a] + 1);
+            }
+            if (budget.fetch_sub(tests, std::memory_order_relaxed) < tests) return;
+            for (int32_t x = c0[0]; x <= c1[0]; ++x)
+                for (int32_t y = c0[1]; y <= c1[1]; ++y)
+                    for (int32_t z = c0[2]; z <= c1[2]; ++z) {
+                        const double c[3] = {x + 0.5, y + 0.5, z + 0.5};
+                        if (triangle_meets_box(p, c, half))
+                            __atomic_store_n(&D[size_t((int64_t(x) * R[1] + y) * R[2] + z)], uint8_t(0), __ATOMIC_RELAXED);
+                    }
+        }
+    });
+    if (budget.load() < 0) return;   // triangles that span very many cells each
+    // Chebyshev distances: two sweeps over the 26 neighbours, 13 before and 13 after
+    // each cell in memory order
+    auto sweep = [&](bool fwd) {
+        for (int64_t i = 0; i < cells; ++i) {
+            const int64_t c = fwd ? i : cells - 1 - i;
+            const int32_t z = int32_t(c % R[2]), y = int32_t(c / R[2] % R[1]), x = int32_t(c / R[2] / R[1]);
+            int best = D[size_t(c)];
+            for (int k = 0; k < 13 && best > 1; ++k) {
+                const int d = fwd ? -1 : 1;
+                const int32_t nx = x + d * (k < 9 ? 1 : 0), ny = y + d * (k < 9 ? k / 3 - 1 : (k < 12 ? 1 : 0)),
+                              nz = z + d * (k < 9 ? k % 3 - 1 : (k < 12 ? k - 10 : 1));
+                if (nx < 0 || ny < 0 || nz < 0 || nx >= R[0] || ny >= R[1] || nz >= R[2]) continue;
+                best = std::min(best, 1 + int(D[size_t((int64_t(nx) * R[1] + ny) * R[2] + nz)]));
+            }
+            D[size_t(c)] = uint8_t(best);
+        }
+    };
+    sweep(true);
+    sweep(false);
+    for (int a = 0; a < 3; ++a) {
+        out->R[a] = R[a];
+        out->clear_inv[a] = inv[a];
+    }
+    out->clear.swap(D);
 }
 
 // Checks of one tet; returns an empty string when it is consistent.
@@ -524,6 +696,7 @@ int pack_mesh(const float* P, int64_t np, const int32_t* tets, const int32_t* nb
                 }
         M.seed.swap(next);
     }
+    clearance_grid(P, tets, nbrs, nt, M.tri_verts_user, lo, hi, &M);
     return TM_OK;
 }
 

@@ -39,6 +39,12 @@ struct PackedMesh {
     int32_t G = 1;
     float lo[3] = {0, 0, 0};
     float inv_cell[3] = {0, 0, 0};
+    // Clearance grid (empty: none): cells of about one tet's size over the bounds.
+    // clear[(x*R1 + y)*R2 + z] is the Chebyshev distance, in cells, from the cell to
+    // the nearest one that a constrained triangle touches (0: this one; at most 255).
+    std::vector<uint8_t> clear;
+    int32_t R[3] = {0, 0, 0};            // cells per axis
+    float clear_inv[3] = {0, 0, 0};      // cells per unit length
 };
 
 // Validate (if requested), renumber along the space-filling curve and build the

@@ -1,0 +1,133 @@
+"""Traces through the clearance grid against the same rays walked from tet to tet
+all the way (asking for step counts selects that walk): the same triangles and
+tets, t and weights bit for bit, for every record layout and every way a ray can
+start."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from synth import kuhn_mesh, pinhole_rays, ao_rays, tri_geometry, random_interior_rays
+
+pytestmark = pytest.mark.gpu
+
+SPHERES = [[0.3, 0.35, 0.4, 0.12], [0.7, 0.6, 0.7, 0.15], [0.55, 0.25, 0.75, 0.08]]
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.fixture(scope="module", params=["tet16", "tet20", "tet32", "tet32n"])
+def scene(request):
+    """24 cells per axis stretched 8 times along x: 137 x 17 x 17 cells of the grid, enough
+    along one axis for secondary rays to use it."""
+    import paper_2103_02309_amd as tetrt
+    m = kuhn_mesh(24, jitter=0.1, seed=5, spheres=SPHERES)
+    m.points = (m.points * np.array([8, 1, 1], np.float32)).astype(np.float32)
+    mesh = tetrt.upload(m.points, m.tets, m.nbrs, m.cflag, layout=request.param)
+    yield m, mesh
+    mesh.free()
+
+
+def _same(mesh, o, d, **kw):
+    kw = {k: _dev(v) if isinstance(v, np.ndarray) else v for k, v in kw.items()}
+    O, D = _dev(o), _dev(d)
+    got = mesh.trace(O, D, want_tets=True, **kw)
+    ref = mesh.trace(O, D, want_tets=True, want_steps=True, **kw)
+    torch.cuda.synchronize()
+    for k in ("tri", "hit_tets", "t", "bary"):
+        a, b = got[k].cpu().numpy(), ref[k].cpu().numpy()
+        assert np.array_equal(a, b, equal_nan=True), (k, int((a != b).sum()), np.nonzero((a != b).reshape(len(o), -1).any(1))[0][:8])
+    return {k: v.cpu().numpy() for k, v in ref.items()}
+
+
+def _interior(n, seed):
+    o, d = random_interior_rays(n, seed)
+    return (o * np.array([8, 1, 1], np.float32)).astype(np.float32), d
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 50001])
+def test_random_rays(scene, n):
+    m, mesh = scene
+    o, d = _interior(n, 7)
+    _same(mesh, o, d)
+    tm = np.random.default_rng(1).uniform(0.0, 3.0, n).astype(np.float32)
+    _same(mesh, o, d * np.float32(0.37), tmax=tm)
+    st = mesh.locate(_dev(o))
+    _same(mesh, o, d, start_tet=st)
+    _same(mesh, o, d, tmax=tm, sort=2)
+
+
+def test_camera_and_secondary_rays(scene):
+    """Camera rays in x, and occlusion rays from their hits (a launch large enough for the
+    grid) with tmax from nothing to past the mesh."""
+    m, mesh = scene
+    o, d, _ = pinhole_rays((0.3, 0.5, 0.5), 160, 120, 40.0, forward=(1.0, 0.0, 0.0))
+    ref = _same(mesh, o, d)
+    hit = ref["tri"] >= 0
+    assert hit.any() and not hit.all()
+    hp = o[hit].astype(np.float64) + ref["t"][hit, None].astype(np.float64) * d[hit]
+    nrm, _ = tri_geometry(m.points, mesh.tri_vertices(ref["tri"][hit]))
+    k = -(-65536 // int(hit.sum()))
+    ao, ad, atm, parent = ao_rays(hp, nrm, d[hit], k=max(8, k), seed=3, tmax=0.4)
+    sf = ref["tri"][hit][parent].astype(np.int32)
+    assert len(ao) >= 65536
+    rng = np.random.default_rng(2)
+    for tmax in (atm, rng.choice(np.array([0.0, 0.01, 0.3, 2.0, np.inf], np.float32), len(ao))):
+        _same(mesh, ao, ad, tmax=tmax, start_face=sf)
+    # some without a start face, one with a triangle that does not exist
+    mix = np.where(rng.random(len(ao)) < 0.3, -1, sf).astype(np.int32)
+    mix[5] = 1 << 30
+    lifted = (hp[parent] + 0.004 * ad).astype(np.float32)
+    _same(mesh, lifted, ad, tmax=atm, start_face=mix)
+
+
+def test_origins_at_and_past_the_bounds(scene):
+    m, mesh = scene
+    o, d = _interior(4000, 9)
+    a = np.random.default_rng(3).integers(0, 3, 4000)
+    hi = np.array([8, 1, 1], np.float32)[a]
+    off = np.tile(np.array([-0.5, -1e-6, 1e-6, 1e-4, 0.01], np.float32), 800)
+    o[np.arange(4000), a] = np.where(np.arange(4000) % 2 == 0, off, hi - off)
+    _same(mesh, o, d)
+
+
+def test_rays_that_are_not_valid(scene):
+    m, mesh = scene
+    o, d = _interior(512, 11)
+    d[::4] = 0.0
+    d[1::8] = np.inf
+    o[2::8, 1] = np.nan
+    d[3::8] *= 1e-25
+    o[5::8, 2] = np.inf
+    st = np.full(512, -1, np.int32)
+    st[6] = m.n_tets
+    tm = np.full(512, 1.0, np.float32)
+    tm[7::16] = np.nan
+    tm[15::16] = -1.0
+    _same(mesh, o, d, tmax=tm, start_tet=st)
+
+
+def test_axis_parallel_rays_against_brute_force(scene):
+    """Directions with zeros (their axis never leaves a box of the grid): the plain
+    definition of the closest hit.  Origins are off the planes of the cells, so no
+    ray meets a vertex or an edge beyond rounding."""
+    from oracle.brute import brute_closest_hit
+    import oracle
+    m, mesh = scene
+    rng = np.random.default_rng(13)
+    o, _ = _interior(600, 13)
+    d = np.zeros((600, 3), np.float32)
+    a = rng.integers(0, 3, 600)
+    d[np.arange(600), a] = np.where(rng.random(600) < 0.5, -1.0, 2.0)
+    d[::3, 1] += np.float32(0.5)
+    d[(d == 0).all(1)] = (1.0, 0.0, 0.0)
+    om = oracle.OracleMesh(m.points, m.tets, m.nbrs, m.cflag)
+    got = mesh.trace(_dev(o), _dev(d))
+    tri, t = brute_closest_hit(m.points, om.tri_verts, o, d)[:2]
+    g = got["tri"].cpu().numpy()
+    assert np.array_equal(g, tri)
+    h = tri >= 0
+    # t is computed in float64 and rounded once to float32
+    assert np.allclose(got["t"].cpu().numpy()[h], t[h], rtol=2.0 ** -23, atol=0)
