@@ -242,15 +242,8 @@ int trace_impl(tm_mesh_s* m, int64_t n_rays, const float* d_orig, const float* d
     c.kernel = o.kernel ? o.kernel : 1;
     c.eps = o.eps;
     // the clearance grid: where no step counts are asked for and the step cap is the
-    // default (both count the steps of a walk all the way).  Secondary rays only in
-    // launches of at least 2^16 rays on grids of at least 128 cells along an axis:
-    // they start among triangles and walk out of them first, so short rays gain
-    // nothing there and pay for the kernel's 7 waves per SIMD instead of 8
-    // (occlusion rays, tmax 0.05 / 0.1: 128 cells per axis and 1.15 M rays 111 -> 96
-    // us / 64 cells 68.4 -> 70.5 us; 4,800 rays 23.6 -> 33.8 us)
-    const float rmax = std::max(m->dev.R[0], std::max(m->dev.R[1], m->dev.R[2]));
-    c.clear = m->dev.clear && !d_steps && !o.fp64_steps && o.max_steps == 0 &&
-              (!d_start_face || (n_rays >= 65536 && rmax >= 128.0f));
+    // default (both count the steps of a walk all the way)
+    c.clear = !d_steps && !o.fp64_steps && o.max_steps == 0 && clear_rule(m, n_rays, d_start_face && d_tmax, 128.0f);
     if (queue) {
         char* base = static_cast<char*>(ws) + perm_bytes;
         c.queue.cursor = reinterpret_cast<uint32_t*>(base);

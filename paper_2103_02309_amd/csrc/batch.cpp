@@ -27,13 +27,14 @@ struct Shape {
     int32_t n_jobs = -1, block = 0, chunk_log2 = 0, layout = -1, xcds = 1;
     int64_t blocks = -1, chunks = -1;
     bool steps = false;   // some job asks for step counts
+    bool clear = false;   // some job's rays use its mesh's clearance grid
     int32_t kernel = 1;   // 1 = one lane per ray, 3 = persistent waves on a queue
     int32_t qchunk = 0, refill = 0;   // kernel 3: rays per wave fetch, refill threshold
     int64_t qchunks = 0;  // kernel 3: chunks over all jobs
     float eps = 0.0f;     // the precision variant (kernel 1)
     bool operator==(const Shape& o) const {
         return n_jobs == o.n_jobs && block == o.block && chunk_log2 == o.chunk_log2 && layout == o.layout &&
-               xcds == o.xcds && blocks == o.blocks && chunks == o.chunks && steps == o.steps &&
+               xcds == o.xcds && blocks == o.blocks && chunks == o.chunks && steps == o.steps && clear == o.clear &&
                kernel == o.kernel && qchunk == o.qchunk && refill == o.refill && qchunks == o.qchunks &&
                eps == o.eps;
     }
@@ -150,6 +151,8 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
         r.fp64_steps = nullptr;
         r.n = j.n_rays;
         r.max_steps = o.max_steps > 0 ? o.max_steps : 65536;
+        J.clear = o.max_steps == 0 && tetrt::clear_rule(j.mesh, j.n_rays, j.d_start_face && j.d_tmax, 64.0f);
+        if (J.clear && j.n_rays > 0) shape->clear = true;
         J.block0 = blocks;
         blocks += (j.n_rays + block - 1) / block;
         J.qchunk0 = qchunks;
@@ -222,7 +225,7 @@ hipError_t enqueue(const tm_batch_s* b, hipStream_t s) {
         return tetrt::launch_trace_batch_queue(b->d_table, sh.n_jobs, q, sh.layout, sh.steps, b->cus, s);
     }
     return tetrt::launch_trace_batch(b->d_table, sh.n_jobs, sh.blocks, sh.block, sh.layout, sh.xcds, sh.steps,
-                                     sh.eps, s);
+                                     sh.clear, sh.eps, s);
 }
 
 int check_batch(const tm_batch_s* b, const char* what) {

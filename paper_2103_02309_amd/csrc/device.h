@@ -133,15 +133,17 @@ struct Job {
     int64_t block0;           // first block of this job in the trace launch
     int64_t chunk0;           // first chunk of this job in the binning launch
     int64_t qchunk0;          // first chunk of this job in the persistent-wave queue
+    int32_t clear;            // nonzero: the rays use the mesh's clearance grid (k_trace_batch_clear)
 };
 
 // One launch over all jobs (table in device memory, block0 ascending); jobs
 // share the record layout.  Rays without tmax get +inf.  xcds > 1: the blocks
 // are renumbered so that each XCD takes one contiguous range of them.  steps:
-// some job has a step-count array (the kernel then keeps per-ray counts).
+// some job has a step-count array (the kernel then keeps per-ray counts).  clear: some
+// job has its `clear` set.
 // eps > 0: the precision variant.
 hipError_t launch_trace_batch(const Job* d_jobs, int32_t n_jobs, int64_t total_blocks, int32_t block,
-                              int32_t layout, int32_t xcds, bool steps, float eps, hipStream_t s);
+                              int32_t layout, int32_t xcds, bool steps, bool clear, float eps, hipStream_t s);
 // The same walk by persistent waves draining the queue q over every job's rays
 // (zeroes q's counters first, with a kernel of its own); `cus` sizes the grid.
 hipError_t launch_trace_batch_queue(const Job* d_jobs, int32_t n_jobs, const Queue& q, int32_t layout,

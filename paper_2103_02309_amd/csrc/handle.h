@@ -47,6 +47,23 @@ inline int32_t xcd_count(int cus) { return cus >= 64 ? cus / 32 : 1; }
 int sort_config(const tm_mesh_s* m, const tm_trace_opts& o, int64_t n, bool has_tmax, SortCfg* c,
                 bool* on);
 
+// Whether n rays use the mesh's clearance grid.  On small meshes a walk is as short
+// as the grid's own chain of loads: at least 56 cells along an axis (camera rays,
+// 24 / 32 / 48 cells of the scene per axis, 34 / 46 / 69 of the grid: 50 k rays
+// 33 -> 46 / 44 -> 43 / 64 -> 51 us, 500 k rays 56 -> 53 / 74 -> 50 / 114 -> 59 us).
+// Secondary rays (those that leave a triangle, with a tmax) start among triangles
+// and walk out of them first, so short ones gain nothing: launches of at least 2^16
+// rays, on grids of at least min_cells cells.  Alone (128 cells): the grid's kernel
+// runs 7 waves per SIMD instead of 8, which short rays pay for (occlusion rays, tmax
+// 0.05: 183 cells per axis and 1.15 M rays 111 -> 96 us, 91 cells 68.4 -> 70.5 us;
+// 183 cells and 4,800 rays 23.6 -> 33.8 us).  In a batch that runs that kernel for
+// its other jobs anyway, 64 cells.
+inline bool clear_rule(const tm_mesh_s* m, int64_t n, bool secondary, float min_cells) {
+    const float* R = m->dev.R;
+    const float most = std::max(R[0], std::max(R[1], R[2]));
+    return m->dev.clear && (secondary ? n >= 65536 && most >= min_cells : most >= 56.0f);
+}
+
 // Room beyond the binning permutation in a fixed workspace (the queue kernel's
 // counters and job entry, the precision variant's tie list).
 constexpr int64_t kFixedExtraBytes = 512 * 1024;

@@ -1157,12 +1157,15 @@ __device__ __forceinline__ Rec walk_begin(const Mem& M, Ray& s) {
 
 // A walking ray looks at the grid from where it crosses the face ahead.  kStop
 // only when the way through empty space is long enough to pay for a restart:
-// t is then where to restart.
+// t is then where to restart.  A walk whose face does not hold the ray strictly
+// goes on walking: it is at an edge, or (a secondary ray whose rounded origin lies
+// outside the triangle that it leaves) beside its line, and keeps its own course.
 template <bool TMAX, int LAYOUT>
 __device__ __forceinline__ March look(const DevMesh& m, const Mem& M, const RayArgs& r, int64_t i, const Ray& s,
                                       float& t) {
     const float l0 = det2(s.w.q1x, s.w.q1y, s.w.q2x, s.w.q2y), l1 = det2(s.w.q2x, s.w.q2y, s.w.q0x, s.w.q0y),
                 l2 = det2(s.w.q0x, s.w.q0y, s.w.q1x, s.w.q1y);
+    if (!(fminf(l0, fminf(l1, l2)) > 0.0f)) return kNear;
     const float il = __builtin_amdgcn_rcpf(l0 + l1 + l2);
     float u = 0.0f;
     if (TMAX) {
@@ -1216,8 +1219,7 @@ __device__ __forceinline__ uint32_t field_of(const DevMesh& m, const Mem& M, int
                             : next_field<kTet20>(R, r, 0u, 0);
 }
 
-// Starts the walk of a ray at its point X = o + t d, a point of the mesh's inside (in
-// empty space, or the ray's origin):
+// Starts the walk of a ray at its point X = o + t d, a point in empty space:
 // hops from the seed tet of X's cell across a face that parts X from the tet until
 // none does, then takes the tet's exit face from the signs of its four vertices'
 // six determinants.  The frame is right-handed about d, so a face seen
@@ -1253,11 +1255,7 @@ __device__ __forceinline__ bool restart_at(const DevMesh& m, const Mem& M, float
         const float sg = copysignf(1.0f, vol);
         w0 *= sg; w1 *= sg; w2 *= sg; w3 *= sg;
         const float lo = fminf(fminf(w0, w1), fminf(w2, w3));
-        if (lo >= 0.0f) {
-            // among triangles (an origin): X has to be well inside the tet
-            if (t == 0.0f && !(lo > 1e-5f * fabsf(vol))) return false;
-            break;
-        }
+        if (lo >= 0.0f) break;
         if (hop == 24 || !(lo < 0.0f)) return false;
         const int j = w0 == lo ? 0 : (w1 == lo ? 1 : (w2 == lo ? 2 : 3));
         int32_t vxn;
@@ -1330,33 +1328,47 @@ __device__ __forceinline__ bool restart_at(const DevMesh& m, const Mem& M, float
     return true;
 }
 
-// A ray's first part, which needs no start tet: a ray that leaves a triangle walks
-// away from it, with a look at the grid now and then, and the others only advance
-// through the grid.  False when the ray's result is written; true when it is to be
-// restarted at t (0: in its origin's cell, which a triangle touches), or (t < 0)
-// the grid is no use to it.
-template <bool TMAX, int LAYOUT>
+// How the rays of a launch start: none on a triangle (the launch has no start_face
+// array), on triangles (a ray without one, among triangles, walks all the way), or
+// either.
+enum Start : int { kStartFree, kStartFace, kStartAny };
+
+// A ray's first part.  One whose origin is in empty space advances through the
+// grid.  The others start as in a mesh without a grid -- on their triangle, or in
+// the tet that holds their origin: among triangles the very choice of the first
+// face can matter to rays that graze an edge, so it is that of setup_ray -- and walk
+// with a look at the grid now and then.  False when the ray's result is written;
+// true when it is to be restarted at t, or (t < 0) the grid is no use to it.
+template <bool TMAX, int LAYOUT, int START>
 __device__ __forceinline__ bool trace_first(const DevMesh& m, const Mem& M, const RayArgs& r, int32_t ray, float& t,
                                             FrameStash& S) {
-    Ray s;
     int64_t i = ray;
-    {
+    if (START == kStartFree || !(r.start_face && r.start_face[i] >= 0)) {
+        const float ox = r.orig[3 * i], oy = r.orig[3 * i + 1], oz = r.orig[3 * i + 2];
+        const float dx = r.dir[3 * i], dy = r.dir[3 * i + 1], dz = r.dir[3 * i + 2];
+        const float tmax = (TMAX && r.tmax) ? r.tmax[i] : INFINITY;
+        // (a ray that is not valid stays with the set-up, which says so)
+        if (ray_valid(ox, oy, oz, dx, dy, dz, tmax) && !(r.start_tet && r.start_tet[i] >= m.nt)) {
+            t = 0.0f;
+            const March w = march(m, ox, oy, oz, dx, dy, dz, tmax, t);
+            if (w == kOut) { write_code(r, i, TM_RAY_MISS, 0); return false; }
+            if (w == kStop) return true;
+        }
+        if (START == kStartFace) { t = -1.0f; return true; }
+    }
+    Ray s;
+    if (START == kStartFace) {
         const float ox = r.orig[3 * i], oy = r.orig[3 * i + 1], oz = r.orig[3 * i + 2];
         const float dx = r.dir[3 * i], dy = r.dir[3 * i + 1], dz = r.dir[3 * i + 2];
         s.tmax = (TMAX && r.tmax) ? r.tmax[i] : INFINITY;
+        s.steps = 0;
         if (!ray_valid(ox, oy, oz, dx, dy, dz, s.tmax)) { write_code(r, i, TM_RAY_INVALID, 0); return false; }
-        const int32_t sf = r.start_face ? r.start_face[i] : -1;
-        if (sf < 0) {
-            if (r.start_tet && r.start_tet[i] >= m.nt) { write_code(r, i, TM_RAY_INVALID, 0); return false; }
-            t = 0.0f;
-            const March w = march(m, ox, oy, oz, dx, dy, dz, s.tmax, t);
-            if (w == kOut) { write_code(r, i, TM_RAY_MISS, 0); return false; }
-            if (w == kOff) t = -1.0f;
-            return true;
-        }
-        if (!setup_on_face<TMAX, LAYOUT, false>(m, M, r, i, sf, ox, oy, oz, dx, dy, dz, s, nullptr)) return false;
+        if (!setup_on_face<TMAX, LAYOUT, false>(m, M, r, i, r.start_face[i], ox, oy, oz, dx, dy, dz, s, nullptr)) return false;
+    } else {
+        RayArgs q = r;
+        if (START == kStartFree) q.start_face = nullptr;
+        if (!setup_ray<TMAX, LAYOUT, false>(m, M, q, i, s, 0.0f)) return false;
     }
-    s.steps = 0;
     stash_frame<TMAX>(S, s);
     Rec R = walk_begin<LAYOUT>(M, s);
     int32_t walked = 0;
@@ -1438,12 +1450,15 @@ __device__ __forceinline__ bool trace_rest(const DevMesh& m, const Mem& M, const
 // The parts follow one another rather than share a loop: what one keeps in
 // registers is then dead in the next (72 registers and no spills; a loop over them
 // took 15 spills more).  The last is for the rays that could not be restarted:
-// they walk all the way, as in a mesh without a grid.
-template <bool TMAX, int LAYOUT>
-__device__ __forceinline__ void trace_clear(const DevMesh& m, const Mem& M, const RayArgs& r, int32_t ray, FrameStash& S) {
+// they walk all the way, as in a mesh without a grid, or (grid = false) for all.
+template <bool TMAX, int LAYOUT, int START>
+__device__ __forceinline__ void trace_clear(const DevMesh& m, const Mem& M, const RayArgs& r, int32_t ray, FrameStash& S,
+                                            bool grid = true) {
     float t;
-    if (!trace_first<TMAX, LAYOUT>(m, M, r, ray, t, S)) return;
-    if (trace_rest<TMAX, LAYOUT>(m, M, r, ray, t, S)) return;
+    if (grid) {
+        if (!trace_first<TMAX, LAYOUT, START>(m, M, r, ray, t, S)) return;
+        if (trace_rest<TMAX, LAYOUT>(m, M, r, ray, t, S)) return;
+    }
     keep(ray);
     const int64_t i = ray;
     Ray s;
@@ -1851,7 +1866,7 @@ k_trace(DevMesh m, RayArgs r, uint32_t xcds, Knobs kn) {
 
 // k_trace for a mesh with a clearance grid, where no step counts are asked for and
 // the step cap is the default.
-template <bool TMAX, int LAYOUT>
+template <bool TMAX, int LAYOUT, int START>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
 k_trace_clear(DevMesh m, RayArgs r, uint32_t xcds, Knobs kn) {
     __shared__ FrameStash S;
@@ -1859,7 +1874,7 @@ k_trace_clear(DevMesh m, RayArgs r, uint32_t xcds, Knobs kn) {
     if (j >= r.n) return;
     const int64_t i = r.perm ? int64_t(r.perm[j]) : j;
     if (uint64_t(i) >= uint64_t(r.n)) return;
-    trace_clear<TMAX, LAYOUT>(m, make_mem<LAYOUT>(m), r, int32_t(i), S);
+    trace_clear<TMAX, LAYOUT, START>(m, make_mem<LAYOUT>(m), r, int32_t(i), S);
 }
 
 // Two-pass precision variant, first pass: the float32 walk with the unsure test
@@ -1984,6 +1999,27 @@ k_trace_batch(const Job* __restrict__ jobs, int32_t n_jobs, uint32_t xcds, float
     if (!setup_ray<true, LAYOUT, false>(m, M, r, i, s, 0.0f)) return;
     walk_ray<true, LAYOUT, STEPS>(M, s, r.max_steps);
     finish_ray<true>(m, M, r, i, s, 0);
+}
+
+// The same launch where some job's rays go through its mesh's clearance grid
+// (Job::clear); the other jobs' rays walk all the way.
+template <int LAYOUT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
+k_trace_batch_clear(const Job* __restrict__ jobs, int32_t n_jobs, uint32_t xcds) {
+    __shared__ FrameStash S;
+    const int64_t b = xcd_block(blockIdx.x, gridDim.x, xcds, 0u);
+    int lo = 0, hi = n_jobs;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (jobs[mid].block0 <= b) lo = mid; else hi = mid;
+    }
+    const DevMesh m = jobs[lo].m;
+    const RayArgs r = jobs[lo].r;
+    const int64_t j = (b - jobs[lo].block0) * blockDim.x + threadIdx.x;
+    if (j >= r.n) return;
+    const int64_t i = r.perm ? int64_t(r.perm[j]) : j;
+    if (uint64_t(i) >= uint64_t(r.n)) return;
+    trace_clear<true, LAYOUT, kStartAny>(m, make_mem<LAYOUT>(m), r, int32_t(i), S, jobs[lo].clear != 0);
 }
 
 // Persistent waves draining a work queue (one launch over one or many jobs).
@@ -2269,8 +2305,13 @@ void launch_trace_t(const DevMesh& m, const RayArgs& r, const LaunchCfg& c, hipS
         hipLaunchKernelGGL((k_trace<TMAX, LAYOUT, false, true>), dim3(unsigned(simple_grid)), dim3(block), 0,
                            s, m, r, uint32_t(std::max(1, c.xcds)), Knobs{0.0f, uint32_t(c.xcd_blocks)});
     } else if (c.clear) {
-        hipLaunchKernelGGL((k_trace_clear<TMAX, LAYOUT>), dim3(unsigned(simple_grid)), dim3(block), 0, s, m, r,
-                           uint32_t(std::max(1, c.xcds)), Knobs{0.0f, uint32_t(c.xcd_blocks)});
+        const Knobs kn{0.0f, uint32_t(c.xcd_blocks)};
+        if (r.start_face)
+            hipLaunchKernelGGL((k_trace_clear<TMAX, LAYOUT, kStartFace>), dim3(unsigned(simple_grid)), dim3(block), 0,
+                               s, m, r, uint32_t(std::max(1, c.xcds)), kn);
+        else
+            hipLaunchKernelGGL((k_trace_clear<TMAX, LAYOUT, kStartFree>), dim3(unsigned(simple_grid)), dim3(block), 0,
+                               s, m, r, uint32_t(std::max(1, c.xcds)), kn);
     } else {
         hipLaunchKernelGGL((k_trace<TMAX, LAYOUT, false, false>), dim3(unsigned(simple_grid)), dim3(block), 0,
                            s, m, r, uint32_t(std::max(1, c.xcds)), Knobs{0.0f, uint32_t(c.xcd_blocks)});
@@ -2298,9 +2339,11 @@ hipError_t launch_trace(const DevMesh& m, const RayArgs& r, const LaunchCfg& c, 
 }
 
 template <int LAYOUT>
-void launch_trace_batch_t(const Job* d_jobs, int32_t n_jobs, dim3 g, dim3 b, uint32_t X, bool steps, float eps,
-                          hipStream_t s) {
-    if (eps > 0.0f)
+void launch_trace_batch_t(const Job* d_jobs, int32_t n_jobs, dim3 g, dim3 b, uint32_t X, bool steps, bool clear,
+                          float eps, hipStream_t s) {
+    if (clear && !steps && !(eps > 0.0f))
+        hipLaunchKernelGGL((k_trace_batch_clear<LAYOUT>), g, b, 0, s, d_jobs, n_jobs, X);
+    else if (eps > 0.0f)
         hipLaunchKernelGGL((k_trace_batch<LAYOUT, true, true>), g, b, 0, s, d_jobs, n_jobs, X, eps);
     else if (steps)
         hipLaunchKernelGGL((k_trace_batch<LAYOUT, true, false>), g, b, 0, s, d_jobs, n_jobs, X, 0.0f);
@@ -2309,14 +2352,14 @@ void launch_trace_batch_t(const Job* d_jobs, int32_t n_jobs, dim3 g, dim3 b, uin
 }
 
 hipError_t launch_trace_batch(const Job* d_jobs, int32_t n_jobs, int64_t total_blocks, int32_t block,
-                              int32_t layout, int32_t xcds, bool steps, float eps, hipStream_t s) {
+                              int32_t layout, int32_t xcds, bool steps, bool clear, float eps, hipStream_t s) {
     const uint32_t X = uint32_t(std::max(1, xcds));
     if (total_blocks <= 0 || n_jobs <= 0) return hipSuccess;
     const dim3 g{unsigned(total_blocks)}, b{unsigned(block)};
-    if (layout == kTet16) launch_trace_batch_t<kTet16>(d_jobs, n_jobs, g, b, X, steps, eps, s);
-    else if (layout == kTet32N) launch_trace_batch_t<kTet32N>(d_jobs, n_jobs, g, b, X, steps, eps, s);
-    else if (layout == kTet32) launch_trace_batch_t<kTet32>(d_jobs, n_jobs, g, b, X, steps, eps, s);
-    else launch_trace_batch_t<kTet20>(d_jobs, n_jobs, g, b, X, steps, eps, s);
+    if (layout == kTet16) launch_trace_batch_t<kTet16>(d_jobs, n_jobs, g, b, X, steps, clear, eps, s);
+    else if (layout == kTet32N) launch_trace_batch_t<kTet32N>(d_jobs, n_jobs, g, b, X, steps, clear, eps, s);
+    else if (layout == kTet32) launch_trace_batch_t<kTet32>(d_jobs, n_jobs, g, b, X, steps, clear, eps, s);
+    else launch_trace_batch_t<kTet20>(d_jobs, n_jobs, g, b, X, steps, clear, eps, s);
     return hipGetLastError();
 }
 

@@ -131,3 +131,45 @@ def test_axis_parallel_rays_against_brute_force(scene):
     h = tri >= 0
     # t is computed in float64 and rounded once to float32
     assert np.allclose(got["t"].cpu().numpy()[h], t[h], rtol=2.0 ** -23, atol=0)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_mixes_meshes_with_and_without(scene, graph):
+    """One launch over a mesh whose rays use the grid (free rays; secondary ones; a mixture
+    of both in one job) and one too small for it, again after a change of rays."""
+    import paper_2103_02309_amd as tetrt
+    m, mesh = scene
+    small = kuhn_mesh(5, jitter=0.1, seed=2, spheres=[[0.5, 0.5, 0.5, 0.3]])
+    layout = {v: k for k, v in tetrt.binding._LAYOUTS.items()}[mesh.info["layout"]]
+    other = tetrt.upload(small.points, small.tets, small.nbrs, small.cflag, layout=layout)
+    b = tetrt.Batch(4, 200000)
+    rng = np.random.default_rng(21)
+    for seed in (31, 32):
+        o, d = _interior(3001, seed)
+        first = mesh.trace(_dev(o), _dev(d))
+        t, tri = first["t"].cpu().numpy(), first["tri"].cpu().numpy()
+        hit = np.resize(np.nonzero(tri >= 0)[0], 70001)
+        so = (o[hit] + t[hit, None] * d[hit]).astype(np.float32)
+        _, sd = random_interior_rays(70001, seed + 5)
+        tm = np.full(70001, 0.5, np.float32)
+        sf = tri[hit].astype(np.int32)
+        po, pd = random_interior_rays(999, seed + 7)
+        rays = [(mesh, o, d, {}), (other, po, pd, {}), (mesh, so, sd, dict(tmax=tm, start_face=sf)),
+                (mesh, so[:5000], sd[:5000], dict(start_face=np.where(rng.random(5000) < 0.5, sf[:5000], -1).astype(np.int32)))]
+        jobs = []
+        for me, ro, rd, kw in rays:
+            jobs.append(dict(mesh=me, orig=_dev(ro), dirs=_dev(rd), out=tetrt.outputs(len(ro), "cuda:0", want_tets=True),
+                             **{k: _dev(v) for k, v in kw.items()}))
+        b.set(jobs)
+        for _ in range(2):
+            for j in jobs:
+                j["out"]["tri"].fill_(-77)
+            (b.graph_launch if graph else b.launch)()
+            torch.cuda.synchronize()
+            for j, (me, ro, rd, kw) in zip(jobs, rays):
+                ref = me.trace(j["orig"], j["dirs"], want_tets=True, want_steps=True, **{k: j[k] for k in kw})
+                for k in ("tri", "hit_tets", "t", "bary"):
+                    a, c = j["out"][k].cpu().numpy(), ref[k].cpu().numpy()
+                    assert np.array_equal(a, c, equal_nan=True), (k, int((a != c).sum()))
+    b.free()
+    other.free()
