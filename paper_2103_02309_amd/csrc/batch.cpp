@@ -107,7 +107,7 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
     table->assign(size_t(n_jobs), tetrt::Job{});
     const int32_t kernel = o.kernel == 3 ? 3 : 1;
     const int32_t qchunk = o.queue_chunk ? o.queue_chunk : 64;
-    int64_t blocks = 0, chunks = 0, rays = 0, perm_at = 0, qchunks = 0;
+    int64_t blocks = 0, chunks = 0, rays = 0, perm_at = 0, qchunks = 0, clear_rays = 0;
     int32_t layout = -1;
     for (int32_t k = 0; k < n_jobs; ++k) {
         const tm_job& j = jobs[k];
@@ -152,7 +152,7 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
         r.n = j.n_rays;
         r.max_steps = o.max_steps > 0 ? o.max_steps : 65536;
         J.clear = o.max_steps == 0 && tetrt::clear_rule(j.mesh, j.n_rays, j.d_start_face && j.d_tmax, 64.0f);
-        if (J.clear && j.n_rays > 0) shape->clear = true;
+        if (J.clear) clear_rays += j.n_rays;
         J.block0 = blocks;
         blocks += (j.n_rays + block - 1) / block;
         J.qchunk0 = qchunks;
@@ -175,6 +175,11 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
     shape->refill = o.refill ? o.refill : (kernel == 3 ? 64 : 16);
     shape->qchunks = qchunks;
     shape->eps = o.eps;
+    // the grid's kernel runs 7 waves per SIMD instead of 8 (precision variant: 4 instead
+    // of 6), which jobs that do not use the grid pay for: where at least a quarter
+    // (half) of the rays use it (bursts of requests, eps 1e-6, a third of their rays in
+    // a mesh with a grid: 737 -> 745 us with that kernel, all of them 876 -> 677 us)
+    shape->clear = clear_rays > 0 && clear_rays * (o.eps > 0.0f ? 2 : 4) >= rays;
     if (kernel == 3 && qchunks >= int64_t(0xFFFFFFFFu))
         return fail(TM_ERR_ARG, "tm_batch_set: too many queue chunks (raise queue_chunk)");
     // automatic: round-robin placement.  One contiguous range per XCD over a

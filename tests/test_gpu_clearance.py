@@ -173,3 +173,51 @@ def test_batch_mixes_meshes_with_and_without(scene, graph):
                     assert np.array_equal(a, c, equal_nan=True), (k, int((a != c).sum()))
     b.free()
     other.free()
+
+
+@pytest.mark.parametrize("eps", [1e-6, 1e-4])
+def test_precision_variant(scene, eps):
+    """Random rays, rays through vertices and along edges, camera and secondary rays with
+    the precision variant: the same triangles and tets as its walk all the way.  t and
+    the weights are float64 values rounded once, from one of two forms (the walk's
+    last face, or the definition where a ray meets a tie): within one unit of float32."""
+    from synth import precision_rays
+    m, mesh = scene
+    po, pd, _ = precision_rays(m.points, m.tets, m.cflag, n=20001, seed=6)
+    po[:16001, 0] *= 8.0   # (the random origins are drawn in the unit cube)
+    o, d, _ = pinhole_rays((0.3, 0.5, 0.5), 96, 64, 40.0, forward=(1.0, 0.0, 0.0))
+    first = mesh.trace(_dev(o), _dev(d), eps=eps)
+    tri, t = first["tri"].cpu().numpy(), first["t"].cpu().numpy()
+    hit = np.resize(np.nonzero(tri >= 0)[0], 70000)
+    so = (o[hit] + t[hit, None] * d[hit]).astype(np.float32)
+    _, sd = random_interior_rays(70000, 8)
+    for ro, rd, kw in ((po, pd, {}), (o, d, {}), (o, d, dict(start_tet=mesh.locate(_dev(o)))),
+                       (so, sd, dict(start_face=_dev(tri[hit]), tmax=_dev(np.full(70000, 0.7, np.float32))))):
+        got = mesh.trace(_dev(ro), _dev(rd), want_tets=True, eps=eps, **kw)
+        ref = mesh.trace(_dev(ro), _dev(rd), want_tets=True, want_steps=True, eps=eps, **kw)
+        torch.cuda.synchronize()
+        for k in ("tri", "hit_tets"):
+            a, b = got[k].cpu().numpy(), ref[k].cpu().numpy()
+            assert np.array_equal(a, b), (k, int((a != b).sum()), np.nonzero((a != b).reshape(len(ro), -1).any(1))[0][:8])
+        for k in ("t", "bary"):
+            a, b = got[k].cpu().numpy(), ref[k].cpu().numpy()
+            assert np.array_equal(np.isnan(a), np.isnan(b))
+            ok = ~np.isnan(b)
+            # a weight near zero comes from a float64 quotient, good to about 1e-12
+            assert np.allclose(a[ok], b[ok], rtol=2.0 ** -22, atol=1e-12 if k == "bary" else 0.0), k
+
+
+def test_precision_batch(scene):
+    """The batched precision variant over a mesh with a grid, against its own walk."""
+    import paper_2103_02309_amd as tetrt
+    m, mesh = scene
+    o, d = _interior(6007, 41)
+    out = tetrt.outputs(6007, "cuda:0", want_tets=True)
+    b = tetrt.Batch(1, 6007)
+    b.set([dict(mesh=mesh, orig=_dev(o), dirs=_dev(d), out=out)], eps=1e-6)
+    b.launch()
+    ref = mesh.trace(_dev(o), _dev(d), want_tets=True, want_steps=True, eps=1e-6)
+    torch.cuda.synchronize()
+    for k in ("tri", "hit_tets", "t", "bary"):
+        assert np.array_equal(out[k].cpu().numpy(), ref[k].cpu().numpy(), equal_nan=True), k
+    b.free()
