@@ -118,7 +118,8 @@ typedef struct {
 typedef struct {
     int32_t max_steps;   /* walk step cap per ray (tets entered); 0 = 65536 */
     int32_t block;       /* threads per block: 64, 128 or 256 (0 = automatic: 256 when the
-                            rays are binned or in a caller's order, else 128) */
+                            rays are binned, in a caller's order or go through the mesh's
+                            clearance grid, else 128) */
     int32_t kernel;      /* 0 = automatic, 1 = one lane per ray, 2 = persistent lanes that
                             take further rays as theirs finish, 3 = persistent waves that
                             drain a work queue: each wave takes chunks of queue_chunk rays
@@ -135,7 +136,8 @@ typedef struct {
                             for binned launches (or with order), off otherwise; 1 = off
                             (the dispatcher's round-robin placement) */
     int32_t sort;        /* ray binning before the walk: 0 = automatic (on for batches of at
-                            least 2^18 rays that carry tmax), 1 = off, 2 = on.  Inside each
+                            least 2^18 rays that carry tmax, unless they go through the mesh's
+                            clearance grid), 1 = off, 2 = on.  Inside each
                             chunk of consecutive rays, rays are grouped by quantised
                             direction, then by the low bits of the Morton index of their
                             origin's cell, and traced in that order; the outputs stay at
@@ -357,7 +359,7 @@ int tm_batch_create(int32_t max_jobs, int64_t max_rays, tm_batch* out);
  * XCDs), eps > 0 (the precision variant, one pass) with kernel 0 or 1 only,
  * xcd_blocks, grid_cap, passes, workspace, fp64_steps and order are ignored, with kernel 1 xcds = 0 means round-robin placement (xcds > 1: one
  * contiguous range of the whole launch per XCD), and the binning chunk size is one for all jobs
- * (sort = 0 bins the jobs that carry tmax and have at least 2^18 rays).  The new table is copied to the device on
+ * (sort = 0 bins the jobs that carry tmax, have at least 2^18 rays and do not go through a clearance grid).  The new table is copied to the device on
  * hip_stream, after the batch's previous table copy has left the staging
  * buffer; launches on that stream that follow see it.  A launch of the batch on
  * another stream must be ordered after this call's stream by the caller.

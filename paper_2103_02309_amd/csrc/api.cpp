@@ -151,6 +151,14 @@ int trace_impl(tm_mesh_s* m, int64_t n_rays, const float* d_orig, const float* d
     int rc = sort_config(m, o, n_rays, d_tmax != nullptr, &sc, &binned);
     if (rc != TM_OK) return rc;
     if (o.order) binned = false;   // the caller's order replaces the call's binning
+    // the clearance grid: one lane per ray, where no step counts are asked for and the
+    // step cap is the default (both count the steps of a walk all the way)
+    const bool clear = o.kernel < 2 && o.passes != 2 && !d_steps && !o.fp64_steps && o.max_steps == 0 &&
+                       clear_rule(m, n_rays, d_start_face && d_tmax, 128.0f);
+    // automatic: rays that go through the grid are not binned.  What binning groups, long
+    // walks in one direction, is mostly skipped (9.95 M occlusion rays of the 12.6M-tet
+    // scene, in image order: 785 / 748 / 986 us binned, 711 / 636 / 928 not)
+    if (clear && o.sort == 0) binned = false;
     const bool queue = o.kernel == 3;
     // workspace: the binning permutation, then (kernel 3) the queue's counters and
     // its one-entry job table
@@ -222,8 +230,11 @@ int trace_impl(tm_mesh_s* m, int64_t n_rays, const float* d_orig, const float* d
     // automatic: 256-thread blocks for binned (or caller-ordered) rays, 128 for
     // the rest, whose walks differ more in length from lane to lane; smaller
     // blocks retire sooner and even out the XCDs' loads (camera rays: 0.834 vs
-    // 0.853 ms; binned AO rays: 1.396 vs 1.340 ms)
-    c.block = o.block ? o.block : ((binned || o.order) ? 256 : 128);
+    // 0.853 ms; binned AO rays: 1.396 vs 1.340 ms).  256 through the grid, whose
+    // kernel's LDS is laid out for 256 threads: smaller blocks leave wave slots empty
+    // (camera 107 vs 110 us, occlusion 708 vs 780, 1 M random rays 222 vs 240, camera
+    // with eps 117 vs 127; LDS sized by the block instead cost 17% on the camera rays)
+    c.block = o.block ? o.block : ((binned || o.order || clear) ? 256 : 128);
     c.cus = m->cus;
     c.waves_per_simd = 8;
     // persistent lanes refill at 16 finished lanes; the queue kernel's waves only once
@@ -241,9 +252,7 @@ int trace_impl(tm_mesh_s* m, int64_t n_rays, const float* d_orig, const float* d
     // measured workload and runs only when asked for)
     c.kernel = o.kernel ? o.kernel : 1;
     c.eps = o.eps;
-    // the clearance grid: where no step counts are asked for and the step cap is the
-    // default (both count the steps of a walk all the way)
-    c.clear = !d_steps && !o.fp64_steps && o.max_steps == 0 && clear_rule(m, n_rays, d_start_face && d_tmax, 128.0f);
+    c.clear = clear;
     if (queue) {
         char* base = static_cast<char*>(ws) + perm_bytes;
         c.queue.cursor = reinterpret_cast<uint32_t*>(base);

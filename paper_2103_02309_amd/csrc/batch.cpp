@@ -107,8 +107,24 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
     table->assign(size_t(n_jobs), tetrt::Job{});
     const int32_t kernel = o.kernel == 3 ? 3 : 1;
     const int32_t qchunk = o.queue_chunk ? o.queue_chunk : 64;
-    int64_t blocks = 0, chunks = 0, rays = 0, perm_at = 0, qchunks = 0, clear_rays = 0;
+    int64_t blocks = 0, chunks = 0, rays = 0, perm_at = 0, qchunks = 0;
     int32_t layout = -1;
+    // the grid's kernel runs 7 waves per SIMD instead of 8 (precision variant: 4 instead
+    // of 6), which jobs that do not use the grid pay for: where at least a quarter
+    // (half) of the rays use it (bursts of requests, eps 1e-6, a third of their rays in
+    // a mesh with a grid: 737 -> 745 us with that kernel, all of them 876 -> 677 us)
+    bool clear = false;
+    if (kernel == 1 && o.max_steps == 0) {
+        int64_t all = 0, use = 0;
+        bool steps = false;
+        for (int32_t k = 0; k < n_jobs; ++k) {
+            all += jobs[k].n_rays;
+            steps = steps || (jobs[k].d_steps && jobs[k].n_rays > 0);
+            if (jobs[k].mesh && tetrt::clear_rule(jobs[k].mesh, jobs[k].n_rays, jobs[k].d_start_face && jobs[k].d_tmax, 64.0f))
+                use += jobs[k].n_rays;
+        }
+        clear = !steps && use > 0 && use * (o.eps > 0.0f ? 2 : 4) >= all;
+    }
     for (int32_t k = 0; k < n_jobs; ++k) {
         const tm_job& j = jobs[k];
         tetrt::Job& J = (*table)[size_t(k)];
@@ -134,6 +150,10 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
         bool binned = false;
         int rc = tetrt::sort_config(j.mesh, o, j.n_rays, j.d_tmax != nullptr, &J.sc, &binned);
         if (rc != TM_OK) return rc;
+        // as in a trace alone: rays that go through the grid are not binned by the
+        // automatic rule
+        J.clear = clear && tetrt::clear_rule(j.mesh, j.n_rays, j.d_start_face && j.d_tmax, 64.0f);
+        if (J.clear && o.sort == 0) binned = false;
         J.m = j.mesh->dev;
         tetrt::RayArgs& r = J.r;
         r.perm = nullptr;
@@ -151,8 +171,6 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
         r.fp64_steps = nullptr;
         r.n = j.n_rays;
         r.max_steps = o.max_steps > 0 ? o.max_steps : 65536;
-        J.clear = o.max_steps == 0 && tetrt::clear_rule(j.mesh, j.n_rays, j.d_start_face && j.d_tmax, 64.0f);
-        if (J.clear) clear_rays += j.n_rays;
         J.block0 = blocks;
         blocks += (j.n_rays + block - 1) / block;
         J.qchunk0 = qchunks;
@@ -175,11 +193,7 @@ int build_table(tm_batch_s* b, int32_t n_jobs, const tm_job* jobs, const tm_trac
     shape->refill = o.refill ? o.refill : (kernel == 3 ? 64 : 16);
     shape->qchunks = qchunks;
     shape->eps = o.eps;
-    // the grid's kernel runs 7 waves per SIMD instead of 8 (precision variant: 4 instead
-    // of 6), which jobs that do not use the grid pay for: where at least a quarter
-    // (half) of the rays use it (bursts of requests, eps 1e-6, a third of their rays in
-    // a mesh with a grid: 737 -> 745 us with that kernel, all of them 876 -> 677 us)
-    shape->clear = clear_rays > 0 && clear_rays * (o.eps > 0.0f ? 2 : 4) >= rays;
+    shape->clear = clear;
     if (kernel == 3 && qchunks >= int64_t(0xFFFFFFFFu))
         return fail(TM_ERR_ARG, "tm_batch_set: too many queue chunks (raise queue_chunk)");
     // automatic: round-robin placement.  One contiguous range per XCD over a
