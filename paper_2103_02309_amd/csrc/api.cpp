@@ -378,7 +378,8 @@ int tetmesh_upload(const float* points, int64_t n_points, const int32_t* tets, c
         (rc = upload_array(m, pm.t_new2old, &d.t_new2old, &cold)) ||
         (rc = upload_array(m, pm.t_old2new, &d.t_old2new, &cold)) ||
         (rc = upload_array(m, pm.seed, &d.seed, &cold)) ||
-        (!pm.clear.empty() && (rc = upload_array(m, pm.clear, &d.clear, &cold)))) {
+        (!pm.clear.empty() && (rc = upload_array(m, pm.clear, &d.clear, &cold))) ||
+        (!pm.fine_seed.empty() && (rc = upload_array(m, pm.fine_seed, &d.fine_seed, &cold)))) {
         release(m);
         delete m;
         return rc;
@@ -415,6 +416,8 @@ int tetmesh_upload(const float* points, int64_t n_points, const int32_t* tets, c
     }
     d.clear_cells = int32_t(pm.clear.size());
     d.clear_passes = pm.R[0] + pm.R[1] + pm.R[2] + 8;
+    if (!pm.clear.empty() && pm.fine_seed.empty()) d.fine_seed = d.seed;
+    d.fine = pm.fine;
     d.G = pm.G;
     d.nt = int32_t(pm.nt);
     d.np = int32_t(pm.np);

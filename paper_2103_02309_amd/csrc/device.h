@@ -24,12 +24,14 @@ struct DevMesh {
     const int32_t* t_old2new; // [nt]
     const int32_t* seed;      // [G^3]
     const uint8_t* clear;     // [R0*R1*R2] clearance grid (pack.h), or null: the mesh has none
+    const int32_t* fine_seed; // start tets of the restarts (fine), or null as clear
     float lo[3];
     float inv_cell[3];
     float clear_inv[3];       // clearance cells per unit length
     float R[3];               // clearance cells per axis
     int32_t clear_cells;      // ... and in all
     int32_t clear_passes;     // cells a ray can cross, at most
+    int32_t fine;             // fine_seed has 2^fine cells for each of seed's per axis
     int32_t G;
     int32_t nt;
     int32_t np;

@@ -379,6 +379,70 @@ uint64_t hilbert_key(uint32_t x, uint32_t y, uint32_t z, int bits) {
     return morton_key(X[0], X[1], X[2], bits);
 }
 
+// A start tet for each cell of a grid of G^3 cells over the bounds: that whose centroid lies
+// nearest to the cell's centre, of those with their centroid in the cell.
+std::vector<int32_t> seed_cells(const PackedMesh& M, int64_t nt, const float lo[3], const float inv[3], int G) {
+    const int64_t ncell = int64_t(G) * G * G;
+    std::vector<int32_t> seed(size_t(ncell), -1);
+    std::vector<double> best(size_t(ncell), std::numeric_limits<double>::infinity());
+    for (int64_t tn = 0; tn < nt; ++tn) {
+        double c[3] = {0, 0, 0};
+        for (int r = 0; r < 4; ++r)
+            for (int a = 0; a < 3; ++a) c[a] += M.pts[3 * (int64_t)M.tetv[4 * tn + r] + a];
+        int ci[3];
+        double d2 = 0;
+        for (int a = 0; a < 3; ++a) {
+            c[a] *= 0.25;
+            double g = (c[a] - lo[a]) * inv[a];
+            ci[a] = std::max(0, std::min(G - 1, int(std::floor(g))));
+            double off = g - (ci[a] + 0.5);
+            d2 += off * off;
+        }
+        int64_t cell = (int64_t(ci[0]) * G + ci[1]) * G + ci[2];
+        if (d2 < best[cell]) {
+            best[cell] = d2;
+            seed[cell] = int32_t(tn);
+        }
+    }
+    // cells that hold no centroid take a face neighbour's seed, those next to a seed
+    // first, then those next to these, and so on
+    const int32_t step[6][3] = {{1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1}};
+    auto side = [&](int64_t cell, const int32_t o[3]) {
+        const int64_t z = cell % G + o[2], y = cell / G % G + o[1], x = cell / G / G + o[0];
+        return x < 0 || y < 0 || z < 0 || x >= G || y >= G || z >= G ? int64_t(-1) : (x * G + y) * G + z;
+    };
+    std::vector<int64_t> at, next;
+    for (int64_t cell = 0; cell < ncell; ++cell)
+        if (seed[cell] < 0) at.push_back(cell);
+    std::vector<int32_t> take;
+    // (the first pass looks at every empty cell, the others at those beside the last)
+    while (!at.empty()) {
+        take.assign(at.size(), -1);
+        for (size_t k = 0; k < at.size(); ++k)
+            for (const auto& o : step) {
+                const int64_t n = side(at[k], o);
+                if (n >= 0 && seed[n] >= 0) {
+                    take[k] = seed[n];
+                    break;
+                }
+            }
+        next.clear();
+        for (size_t k = 0; k < at.size(); ++k)
+            if (take[k] >= 0) seed[at[k]] = take[k];
+        for (size_t k = 0; k < at.size(); ++k)
+            if (take[k] >= 0)
+                for (const auto& o : step) {
+                    const int64_t n = side(at[k], o);
+                    if (n >= 0 && seed[n] == -1) {
+                        seed[n] = -2;   // in the list for the next pass
+                        next.push_back(n);
+                    }
+                }
+        at.swap(next);
+    }
+    return seed;
+}
+
 int pack_mesh(const float* P, int64_t np, const int32_t* tets, const int32_t* nbrs,
               const uint8_t* cflag, int64_t nt, const tm_upload_opts& opts, PackedMesh* out,
               std::string* err) {
@@ -651,52 +715,16 @@ int pack_mesh(const float* P, int64_t np, const int32_t* tets, const int32_t* nb
         double e = double(hi[a]) - lo[a];
         M.inv_cell[a] = e > 0 ? float(G / e) : 0.0f;
     }
-    const int64_t ncell = int64_t(G) * G * G;
-    M.seed.assign(size_t(ncell), -1);
-    std::vector<double> best(size_t(ncell), std::numeric_limits<double>::infinity());
-    for (int64_t tn = 0; tn < nt; ++tn) {
-        double c[3] = {0, 0, 0};
-        for (int r = 0; r < 4; ++r)
-            for (int a = 0; a < 3; ++a) c[a] += M.pts[3 * (int64_t)M.tetv[4 * tn + r] + a];
-        int ci[3];
-        double d2 = 0;
-        for (int a = 0; a < 3; ++a) {
-            c[a] *= 0.25;
-            double g = (c[a] - lo[a]) * M.inv_cell[a];
-            ci[a] = std::max(0, std::min(G - 1, int(std::floor(g))));
-            double off = g - (ci[a] + 0.5);
-            d2 += off * off;
-        }
-        int64_t cell = (int64_t(ci[0]) * G + ci[1]) * G + ci[2];
-        if (d2 < best[cell]) {
-            best[cell] = d2;
-            M.seed[cell] = int32_t(tn);
-        }
-    }
-    // cells that hold no centroid take a face neighbour's seed
-    for (bool changed = true; changed;) {
-        changed = false;
-        std::vector<int32_t> next = M.seed;
-        for (int x = 0; x < G; ++x)
-            for (int y = 0; y < G; ++y)
-                for (int z = 0; z < G; ++z) {
-                    int64_t cell = (int64_t(x) * G + y) * G + z;
-                    if (M.seed[cell] >= 0) continue;
-                    const int d[6][3] = {{1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1}};
-                    for (auto& o : d) {
-                        int a = x + o[0], b = y + o[1], c = z + o[2];
-                        if (a < 0 || b < 0 || c < 0 || a >= G || b >= G || c >= G) continue;
-                        int32_t s = M.seed[(int64_t(a) * G + b) * G + c];
-                        if (s >= 0) {
-                            next[cell] = s;
-                            changed = true;
-                            break;
-                        }
-                    }
-                }
-        M.seed.swap(next);
-    }
+    M.seed = seed_cells(M, nt, lo, M.inv_cell, G);
     clearance_grid(P, tets, nbrs, nt, M.tri_verts_user, lo, hi, &M);
+    if (!M.clear.empty()) {
+        M.fine = G <= 128 ? 1 : 0;
+        if (M.fine) {
+            float inv[3];
+            for (int a = 0; a < 3; ++a) inv[a] = 2.0f * M.inv_cell[a];
+            M.fine_seed = seed_cells(M, nt, lo, inv, 2 * G);
+        }
+    }
     return TM_OK;
 }
 

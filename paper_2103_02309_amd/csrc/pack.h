@@ -45,6 +45,12 @@ struct PackedMesh {
     std::vector<uint8_t> clear;
     int32_t R[3] = {0, 0, 0};            // cells per axis
     float clear_inv[3] = {0, 0, 0};      // cells per unit length
+    // Start tets of the walks that start anew behind empty space: a seed grid of twice
+    // the cells per axis, about one per cube of six tets (fine = 1), or seed itself where
+    // that has more than 128 (fine = 0, fine_seed empty).  Rays that name no start tet
+    // keep to seed, whose choice their results can show.
+    std::vector<int32_t> fine_seed;
+    int32_t fine = 0;
 };
 
 // Validate (if requested), renumber along the space-filling curve and build the

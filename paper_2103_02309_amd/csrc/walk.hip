@@ -1076,8 +1076,8 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb, uint32_t 
 // ray's 2-D origin strictly, in the walk's own arithmetic, so it joins the chain
 // that the walk from the origin follows: the results are the same, bit for bit.
 // Measured, one MI355X, before and after: 2.07 M camera rays of the 12.6M-tet scene
-// 0.95 -> 0.11 ms; their 9.95 M occlusion rays (tmax 0.1, with binning) 1.27 -> 0.77
-// ms; 1 M rays between random points of 1.57 M tets 1.89 -> 0.19 ms.
+// 0.95 -> 0.10 ms; their 9.95 M occlusion rays (tmax 0.1; 1.27 with binning) 0.71
+// ms; 1 M rays between random points of 1.57 M tets 1.89 -> 0.20 ms.
 // Positions are good to about 1e-5 cells and triangles mark the cells within
 // 4e-3 of them (pack.cpp), so a position kMarchStep past a box's border, which
 // settles the cell ahead, has skipped no triangle and is still in empty space.
@@ -1232,10 +1232,16 @@ template <bool TMAX, int LAYOUT, bool EXACT = false>
 __device__ __forceinline__ bool restart_at(const DevMesh& m, const Mem& M, float ox, float oy, float oz, float dx,
                                            float dy, float dz, float t, Ray& s, FrameStash& S) {
     const float X = fmaf(t, dx, ox), Y = fmaf(t, dy, oy), Z = fmaf(t, dz, oz);
-    const int cx = min(max(int(floorf((X - m.lo[0]) * m.inv_cell[0])), 0), m.G - 1);
-    const int cy = min(max(int(floorf((Y - m.lo[1]) * m.inv_cell[1])), 0), m.G - 1);
-    const int cz = min(max(int(floorf((Z - m.lo[2]) * m.inv_cell[2])), 0), m.G - 1);
-    int32_t tet = m.seed[(cx * m.G + cy) * m.G + cz];
+    // the finer seed grid: fewer hops, each three dependent loads (cells of two cubes of
+    // six tets, then of one: camera rays 106 -> 98 us, 1 M random rays 224 -> 205,
+    // camera rays with eps 135 -> 125; cells of 0.7 such cubes, a table of 25 MB: no
+    // better than one)
+    const int32_t* seeds = m.fine_seed;
+    const int F = m.G << m.fine;
+    auto cell = [&](float x, int a) {
+        return min(max(int(floorf((x - m.lo[a]) * m.inv_cell[a] * 2.0f)) >> (1 - m.fine), 0), F - 1);
+    };
+    int32_t tet = seeds[(cell(X, 0) * F + cell(Y, 1)) * F + cell(Z, 2)];
     int4 v;
     float4 P0, P1, P2, P3;
     float vol;

@@ -221,3 +221,17 @@ def test_precision_batch(scene):
     for k in ("tri", "hit_tets", "t", "bary"):
         assert np.array_equal(out[k].cpu().numpy(), ref[k].cpu().numpy(), equal_nan=True), k
     b.free()
+
+
+@pytest.mark.parametrize("seed_grid", [1, 2, 128, 129])
+def test_restart_seeds(seed_grid):
+    """The start tets of the restarts: coarse ones that take many hops or too many, and on
+    both sides of the line where the call's own seed grid serves."""
+    import paper_2103_02309_amd as tetrt
+    m = kuhn_mesh(24, jitter=0.1, seed=5, spheres=SPHERES)
+    m.points = (m.points * np.array([8, 1, 1], np.float32)).astype(np.float32)
+    mesh = tetrt.upload(m.points, m.tets, m.nbrs, m.cflag, seed_grid=seed_grid)
+    o, d = _interior(20001, 17)
+    _same(mesh, o, d, start_tet=mesh.locate(_dev(o)))
+    _same(mesh, o, d, tmax=np.full(20001, 2.0, np.float32))
+    mesh.free()
